@@ -17,7 +17,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libhetpipe.so")
-SOURCES = ["igemm.hip", "elementwise.hip", "wsp.hip", "hetpipe.cpp"]
+SOURCES = ["igemm.hip", "igemm_split.hip", "elementwise.hip", "wsp.hip", "hetpipe.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
@@ -33,7 +33,8 @@ CFLAGS = [
 EXTRA = {"wsp.hip": ["-ffp-contract=off"]}
 
 
-HEADERS = [os.path.join(CSRC, "kernels.h"), os.path.join(ROOT, "include", "hetpipe.h")]
+HEADERS = [os.path.join(CSRC, "kernels.h"), os.path.join(CSRC, "igemm_common.h"),
+           os.path.join(ROOT, "include", "hetpipe.h")]
 
 
 def _stale(src: str, obj: str) -> bool:

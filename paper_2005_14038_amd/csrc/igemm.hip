@@ -28,495 +28,16 @@
 // fan-in) and layers with too few output tiles to fill the chip are cut into
 // chunks; each chunk writes a partial tile to a workspace and a second kernel
 // adds the partials in a fixed order, so results are deterministic.
-#include <type_traits>
-
-#include "kernels.h"
+#include "igemm_common.h"
 
 namespace hp {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
 namespace {
 
-// LDS row padding (floats).  Operands staged from k-major rows are written
-// transposed, one float per store: a row length of 2 mod 32 spreads a wave's
-// stores over distinct banks.  Operands staged as whole float4 rows need a
-// row length that keeps 16-byte alignment.
-constexpr int PAD_T = 2;
-constexpr int PAD_V = 4;
-
-// Tile configurations: workgroup tile BM x BN, reduction tile BK of the
-// kernels that stage from fp32 and BKH of the kernels on bf16 operands in
-// memory, wave tile WM x WN (a grid of (WM/32) x (WN/32) MFMA 32x32 tiles per
-// wave); the workgroup has (BM/WM) * (BN/WN) waves.  BKH = 64 halves the
-// barriers per MFMA; the 128x64 tile keeps 32, where the second register set
-// of a 64-wide k tile would cost it occupancy.
-struct TileCfg { int bm, bn, bk, wm, wn, bkh; };
-// Waves of 32x64 (eight in the general tile, four in the 128x64 and 64x128
-// ones) hide the staging latency better than fewer waves of 64x64, at the
-// cost of more LDS reads per MFMA.
-constexpr TileCfg kCfgs[] = {
-    {128, 128, 16, 32, 64, 64},    // 0: general (8 waves)
-    {128, 64, 16, 32, 64, 32},     // 1: narrow N (at most 64 output columns, 4 waves)
-    {64, 256, 16, 64, 64, 32},     // 2: narrow M, N a multiple of 256 or large
-    {64, 128, 16, 32, 64, 64},     // 3: narrow M otherwise (4 waves)
-    {64, 64, 16, 32, 32, 64},      // 4: small M and N (4 waves of 32x32)
-    {256, 128, 16, 128, 64, 32},   // 5: igemm_h16d_kernel (4 waves)
-};
-
-struct KArgs {
-    ConvGeo g;
-    const float* a;
-    const float* b;
-    float* out;
-    const float* bias;
-    const float* mask;
-    float* bias_out;
-    long M, Ncols, Kred;
-    int tiles_m, tiles_n;
-    int tfull;        // tiles computed whole, one per workgroup (the first tfull ids)
-    int splits;       // every remaining tile is cut into `splits` reduction chunks
-    int kchunk;       // reduction length of a chunk (multiple of the K tile)
-    float* ws;        // partial tiles of the cut tiles: [tile - tfull][split][BM * BN]
-    float* stats;     // optional column statistics per row tile (see Epilogue)
-    int epi;
-    const unsigned short* a16;   // bf16 copies of a and b (16-bit operand kernel only)
-    const unsigned short* b16;
-    // optional: every final output element is also written here rounded to
-    // bf16 (nearest even), row-major like out (no bias-gradient column)
-    unsigned short* out16;
-    // weight gradient on bf16 operands: floor(i / Q) = (i * mq) >> sq and
-    // floor(i / P) = (i * mp) >> sp for 0 <= i < 2^31
-    unsigned mq, mp;
-    int sq, sp;
-};
-
-// Destination of output element (row, col): the bias-gradient column of a
-// weight gradient goes to bias_out[row]; everything else is row-major with
-// the weight part's row length.
-__device__ __forceinline__ float* out_ptr(float* out, float* bias_out, long row, long col,
-                                          long Ncols, int epi) {
-    if (epi & EPI_BIASCOL) {
-        if (col == Ncols - 1) return bias_out + row;
-        return out + row * (Ncols - 1) + col;
-    }
-    return out + row * Ncols + col;
-}
-
-__device__ __forceinline__ float epilogue(float v, long row, long col, long Ncols, int epi,
-                                          const float* bias, const float* mask, const float* prev) {
-    if (epi & EPI_BIAS) v += bias[col];
-    if (epi & EPI_RELU) v = fmaxf(v, 0.f);
-    if ((epi & EPI_MASK) && !(mask[row * Ncols + col] > 0.f)) v = 0.f;
-    if (epi & EPI_ACCUM) v += *prev;
-    return v;
-}
-
-__device__ __forceinline__ float round_bf16(float x) {
-    unsigned u = __float_as_uint(x);
-    u = (u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u;
-    return __uint_as_float(u);
-}
-
-// Two floats rounded to bf16, packed low element first (LDS byte order).
-__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
-    return (__float_as_uint(round_bf16(lo)) >> 16) | (__float_as_uint(round_bf16(hi)) & 0xFFFF0000u);
-}
-
-__device__ __forceinline__ unsigned short bf16_bits(float x) {
-    return (unsigned short)(__float_as_uint(round_bf16(x)) >> 16);
-}
-
-// Work assignment.  The first `tfull` workgroups each compute one whole
-// output tile (whole rounds of the resident workgroups); the rest cut each
-// remaining tile's reduction into `splits` chunks, so that the last round is
-// as full as the others, and leave partial tiles for the reduce kernels.
-// XCD-aware: consecutive workgroup ids are dealt round-robin to the 8 XCDs;
-// each XCD gets a contiguous run of whole tiles (n fastest), so tiles sharing
-// A rows share that XCD's L2, and likewise a contiguous run of cut-tile items
-// (chunk, tile), so tiles reducing over the same chunk share it.
-struct Work {
-    int tile, z;
-    bool partial;
-    long m0, n0, kbeg, kend;
-};
-
-template <int BM, int BN>
-__device__ __forceinline__ Work decode_work(const KArgs& args) {
-    Work w;
-    int bid = blockIdx.x;
-    w.z = 0;
-    w.partial = bid >= args.tfull;
-    if (!w.partial) {
-        if ((args.tfull & 7) == 0) bid = (bid & 7) * (args.tfull >> 3) + (bid >> 3);
-        w.tile = bid;
-    } else {
-        const int r = bid - args.tfull;
-        const int ncut = args.tiles_m * args.tiles_n - args.tfull;
-        if ((args.tfull & 7) == 0) {
-            // the workgroups of one XCD (ids congruent mod 8) take a contiguous
-            // run of (chunk, tile) items, tiles fastest: the cut tiles that
-            // reduce over the same chunk (same dy rows, same image rows) share
-            // that XCD's L2
-            const int nparts = ncut * args.splits;
-            const int x = r & 7, q = nparts >> 3, rem = nparts & 7;
-            const int item = x * q + min(x, rem) + (r >> 3);
-            w.z = item / ncut;
-            w.tile = args.tfull + (item - w.z * ncut);
-        } else {
-            w.tile = args.tfull + r / args.splits;
-            w.z = r - (w.tile - args.tfull) * args.splits;
-        }
-    }
-    w.m0 = (long)(w.tile / args.tiles_n) * BM;
-    w.n0 = (long)(w.tile % args.tiles_n) * BN;
-    w.kbeg = w.partial ? (long)w.z * args.kchunk : 0;
-    w.kend = w.partial ? min(w.kbeg + (long)args.kchunk, args.Kred) : args.Kred;
-    return w;
-}
-
-// Writes a wave's accumulators: acc[i][j][v] holds
-// out[m0 + wm + 32i + 8(v/4) + 4(lane/32) + v%4][n0 + wn + 32j + lane%32]
-// (the output layout of the 32x32 MFMAs), through the epilogue, or raw into
-// the workspace slot of a cut tile.  The epilogue's reads (the previous
-// output to accumulate into, the ReLU mask) of one 32x32 tile are all issued
-// before its stores: a store may alias a later read as far as the compiler
-// knows, so interleaving them would serialise one memory latency per element.
-constexpr int EPI_CHUNK = 8;     // outputs per lane whose epilogue reads are batched
-
-template <int BM, int BN, int TM, int TN, bool FENCE = false>
-__device__ __forceinline__ void store_tile(const KArgs& args, const Work& w,
-                                           const floatx16 (&acc)[TM][TN], int wm, int wn,
-                                           int lane) {
-    const int lr = lane & 31, lk = lane >> 5;
-    if (w.partial) {
-        float* pslot = args.ws + ((long)(w.tile - args.tfull) * args.splits + w.z) * (BM * BN);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-                if constexpr (FENCE) __builtin_amdgcn_sched_barrier(0);   // one block at a time
-            const int lcol = wn + 32 * j + lr;
-            if (w.n0 + lcol >= args.Ncols) continue;
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int lrow = wm + 32 * i + 8 * (v >> 2) + 4 * lk + (v & 3);
-                    if (w.m0 + lrow < args.M) pslot[lrow * BN + lcol] = acc[i][j][v];
-                }
-        }
-        return;
-    }
-    const int epi = args.epi;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const long col = w.n0 + wn + 32 * j + lr;
-        if (col >= args.Ncols) continue;
-        // output row stride and the address of (row0, col); the bias-gradient
-        // column goes to bias_out[row]
-        long ld = args.Ncols;
-        float* cbase = args.out + col;
-        if (epi & EPI_BIASCOL) {
-            ld = args.Ncols - 1;
-            cbase = args.out + col;
-            if (col == args.Ncols - 1) { ld = 1; cbase = args.bias_out; }
-        }
-        const float bias = (epi & EPI_BIAS) ? args.bias[col] : 0.f;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            if constexpr (FENCE) __builtin_amdgcn_sched_barrier(0);   // one block at a time
-            const long row0 = w.m0 + wm + 32 * i + 4 * lk;
-            // rows row0 + 8(v/4) + v%4 of this lane; those >= M are outside
-            const int left = (int)min(args.M - row0, 32L);
-            float* obase = cbase + row0 * ld;
-            const float* mbase = (epi & EPI_MASK) ? args.mask + row0 * args.Ncols + col : nullptr;
-            const int ldi = (int)ld, ldm = (int)args.Ncols;
-#pragma unroll
-            for (int v0 = 0; v0 < 16; v0 += EPI_CHUNK) {
-                float prev[EPI_CHUNK], msk[EPI_CHUNK];
-#pragma unroll
-                for (int u = 0; u < EPI_CHUNK; ++u) {
-                    const int r = 8 * ((v0 + u) >> 2) + ((v0 + u) & 3);
-                    prev[u] = 0.f;
-                    msk[u] = 1.f;
-                    if (r < left) {
-                        if (epi & EPI_ACCUM) prev[u] = obase[r * ldi];
-                        if (epi & EPI_MASK) msk[u] = mbase[r * ldm];
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < EPI_CHUNK; ++u) {
-                    const int r = 8 * ((v0 + u) >> 2) + ((v0 + u) & 3);
-                    if (r >= left) continue;
-                    float val = acc[i][j][v0 + u];
-                    if (epi & EPI_BIAS) val += bias;
-                    if (epi & EPI_RELU) val = fmaxf(val, 0.f);
-                    if ((epi & EPI_MASK) && !(msk[u] > 0.f)) val = 0.f;
-                    if (epi & EPI_ACCUM) val += prev[u];
-                    obase[r * ldi] = val;
-                    if (args.out16) args.out16[(row0 + r) * args.Ncols + col] = bf16_bits(val);
-                }
-            }
-        }
-    }
-}
-
-// The same writes through the wave's private 4 KB LDS slot (the k loop's
-// buffers are free once its last barrier has passed): each 32x32 block is
-// staged in LDS and read back with every lane holding 4 consecutive columns of
-// one row (8 rows per pass, 4 passes, two at a time), so the epilogue's loads and stores are
-// 16 bytes wide instead of 4.  Used when the output, the bias and the mask
-// allow 16-byte access and there is no bias-gradient column; a group of 4
-// columns that crosses the last column is written element by element.
-constexpr int SLOT_FLOATS = 32 * 32;
-
-template <int BM, int BN, int TM, int TN, bool FENCE = false>
-__device__ __forceinline__ void store_tile_wide(const KArgs& args, const Work& w,
-                                                const floatx16 (&acc)[TM][TN], int wm, int wn,
-                                                int lane, float* slot) {
-    const int lr = lane & 31, lk = lane >> 5;
-    const int rq = lane >> 3, cq = (lane & 7) * 4;
-    const int epi = args.epi;
-    const long N = args.Ncols;
-    float* pslot =
-        w.partial ? args.ws + ((long)(w.tile - args.tfull) * args.splits + w.z) * (BM * BN)
-                  : nullptr;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            if constexpr (FENCE) __builtin_amdgcn_sched_barrier(0);   // one block at a time
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                slot[(8 * (v >> 2) + 4 * lk + (v & 3)) * 32 + lr] = acc[i][j][v];
-            const int lcol = wn + 32 * j + cq;
-            const long col = w.n0 + lcol;
-            const bool full = col + 3 < N;
-            float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (!w.partial && (epi & EPI_BIAS) && col < N) {
-                if (full) {
-                    bias = *reinterpret_cast<const float4*>(args.bias + col);
-                } else {
-                    bias.x = args.bias[col];
-                    if (col + 1 < N) bias.y = args.bias[col + 1];
-                    if (col + 2 < N) bias.z = args.bias[col + 2];
-                }
-            }
-            // two passes (rows 8q + rq) at a time: their epilogue reads first,
-            // then the stores
-#pragma unroll
-            for (int q0 = 0; q0 < 4; q0 += 2) {
-                float4 val[2];
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    val[h] = *reinterpret_cast<const float4*>(slot + (8 * (q0 + h) + rq) * 32 + cq);
-                if (w.partial) {
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int lrow = wm + 32 * i + 8 * (q0 + h) + rq;
-                        if (w.m0 + lrow < args.M && col < N)
-                            *reinterpret_cast<float4*>(pslot + lrow * BN + lcol) = val[h];
-                    }
-                    continue;
-                }
-                if (col >= N) continue;
-                float4 prev[2], msk[2];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const long row = w.m0 + wm + 32 * i + 8 * (q0 + h) + rq;
-                    prev[h] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    msk[h] = make_float4(1.f, 1.f, 1.f, 1.f);
-                    if (row >= args.M) continue;
-                    const long off = row * N + col;
-                    if (full) {
-                        if (epi & EPI_ACCUM) prev[h] = *reinterpret_cast<const float4*>(args.out + off);
-                        if (epi & EPI_MASK) msk[h] = *reinterpret_cast<const float4*>(args.mask + off);
-                    } else {
-                        float* pp = &prev[h].x;
-                        float* mm = &msk[h].x;
-                        for (int e = 0; e < 4 && col + e < N; ++e) {
-                            if (epi & EPI_ACCUM) pp[e] = args.out[off + e];
-                            if (epi & EPI_MASK) mm[e] = args.mask[off + e];
-                        }
-                    }
-                }
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const long row = w.m0 + wm + 32 * i + 8 * (q0 + h) + rq;
-                    if (row >= args.M) continue;
-                    float o[4] = {val[h].x, val[h].y, val[h].z, val[h].w};
-                    const float b4[4] = {bias.x, bias.y, bias.z, bias.w};
-                    const float p4[4] = {prev[h].x, prev[h].y, prev[h].z, prev[h].w};
-                    const float m4[4] = {msk[h].x, msk[h].y, msk[h].z, msk[h].w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (epi & EPI_BIAS) o[e] += b4[e];
-                        if (epi & EPI_RELU) o[e] = fmaxf(o[e], 0.f);
-                        if ((epi & EPI_MASK) && !(m4[e] > 0.f)) o[e] = 0.f;
-                        if (epi & EPI_ACCUM) o[e] += p4[e];
-                    }
-                    const long off = row * N + col;
-                    if (full) {
-                        *reinterpret_cast<float4*>(args.out + off) =
-                            make_float4(o[0], o[1], o[2], o[3]);
-                        if (args.out16) {
-                            uint2 h;
-                            h.x = pack_bf16(o[0], o[1]);
-                            h.y = pack_bf16(o[2], o[3]);
-                            *reinterpret_cast<uint2*>(args.out16 + off) = h;
-                        }
-                    } else {
-                        for (int e = 0; e < 4 && col + e < N; ++e) {
-                            args.out[off + e] = o[e];
-                            if (args.out16) args.out16[off + e] = bf16_bits(o[e]);
-                        }
-                    }
-                }
-            }
-        }
-    }
-}
-
-// Column statistics of a whole tile for a following batch norm: the mean of
-// each column over the tile's rows below M and the sum of squared deviations
-// from it, two passes over the accumulators (values after the bias), lanes l
-// and l + 32 combined by a shuffle, the waves along M through LDS in a fixed
-// order.  Every thread of the workgroup takes part (barriers); lds holds at
-// least (BM / WM + 1) * BN floats.
-template <int BM, int BN, int TM, int TN>
-__device__ __forceinline__ void tile_stats(const KArgs& args, const Work& w,
-                                           const floatx16 (&acc)[TM][TN], int wm, int wn,
-                                           int lane, float* lds) {
-    constexpr int WAVES_M = BM / (32 * TM);
-    const int lr = lane & 31, lk = lane >> 5;
-    const int wave_m = wm / (32 * TM);
-    const long rows = min((long)BM, args.M - w.m0);
-    float* part = lds;                   // [WAVES_M][BN]
-    float* mean = lds + WAVES_M * BN;    // [BN]
-    const int t = threadIdx.x;
-    const int nthreads = blockDim.x;
-    float bias[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const long col = w.n0 + wn + 32 * j + lr;
-        bias[j] = ((args.epi & EPI_BIAS) && col < args.Ncols) ? args.bias[col] : 0.f;
-    }
-    for (int pass = 0; pass < 2; ++pass) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const float mu = pass ? mean[wn + 32 * j + lr] : 0.f;
-            float sum = 0.f;
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int r = wm + 32 * i + 8 * (v >> 2) + 4 * lk + (v & 3);
-                    if (r < rows) {
-                        const float d = acc[i][j][v] + bias[j] - mu;
-                        sum += pass ? d * d : d;
-                    }
-                }
-            sum += __shfl_xor(sum, 32);
-            if (lk == 0) part[wave_m * BN + wn + 32 * j + lr] = sum;
-        }
-        __syncthreads();
-        for (int c = t; c < BN; c += nthreads) {
-            float s = 0.f;
-            for (int m = 0; m < WAVES_M; ++m) s += part[m * BN + c];
-            const long col = w.n0 + c;
-            if (pass == 0) {
-                mean[c] = rows > 0 ? s / (float)rows : 0.f;
-            } else if (col < args.Ncols) {
-                const long tm = w.m0 / BM;
-                args.stats[tm * args.Ncols + col] = mean[c];
-                args.stats[((long)args.tiles_m + tm) * args.Ncols + col] = s;
-            }
-        }
-        __syncthreads();
-    }
-}
-
-// Writes a wave's tile: the wide path when the kernel was built with it
-// (WIDE) and its conditions hold (uniform).  The wide path costs registers,
-// which the fp32 kernels on long reductions, where the epilogue is a small
-// part of the time, keep for occupancy.
-// The epilogue without column statistics: the wide path where the output, the
-// bias, the mask and the workspace allow 16-byte access and there is no
-// bias-gradient column, else the narrow one.
-template <int BM, int BN, int TM, int TN, bool FENCE = false>
-__device__ __forceinline__ void write_tile_plain(const KArgs& args, const Work& w,
-                                                 const floatx16 (&acc)[TM][TN], int wm, int wn,
-                                                 int lane, float* slot) {
-    auto a16 = [](const void* p) { return (((uintptr_t)p) & 15) == 0; };
-    const int epi = args.epi;
-    const bool wide = !(epi & EPI_BIASCOL) && (args.Ncols & 3) == 0 && a16(args.out) &&
-                      (!(epi & EPI_BIAS) || a16(args.bias)) &&
-                      (!(epi & EPI_MASK) || a16(args.mask)) && a16(args.ws);
-    if (wide)
-        store_tile_wide<BM, BN, TM, TN, FENCE>(args, w, acc, wm, wn, lane, slot);
-    else
-        store_tile<BM, BN, TM, TN, FENCE>(args, w, acc, wm, wn, lane);
-}
-
-template <int BM, int BN, int TM, int TN, bool WIDE = true>
-__device__ __forceinline__ void write_tile(const KArgs& args, const Work& w,
-                                           const floatx16 (&acc)[TM][TN], int wm, int wn,
-                                           int lane, float* slot, float* lds_all) {
-    if constexpr (WIDE) {
-        // column statistics of whole tiles (uniform per workgroup: it is either
-        // whole or cut); the LDS slots are reused afterwards.  Built only into
-        // the wide kernels, whose register budget already allows it.
-        if (args.stats && !w.partial)
-            tile_stats<BM, BN, TM, TN>(args, w, acc, wm, wn, lane, lds_all);
-        write_tile_plain<BM, BN, TM, TN>(args, w, acc, wm, wn, lane, slot);
-        return;
-    }
-    store_tile<BM, BN, TM, TN>(args, w, acc, wm, wn, lane);
-}
-
-// Raw buffer loads: the hardware's range check returns zeros for an offset at
-// or past the end of the buffer, so an operand element that lies in the
-// padding or outside the matrix is read with an offset of BUF_OOB instead of
-// being masked.
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-constexpr unsigned BUF_OOB = 0x80000000u;      // buffer offset past any operand here
-constexpr int BUF_CFG = 0x00020000;            // buffer descriptor word 3 (gfx9 family)
-
-__device__ __forceinline__ uintx4 buf_load16(__amdgpu_buffer_rsrc_t rs, unsigned voff,
-                                             unsigned soff) {
-    return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (int)soff, 0);
-}
-
-// ---- operand gathers -------------------------------------------------------
-// Each returns VW consecutive elements along the operand's contiguous axis
-// (zero where the element lies outside the problem or in the padding).
-
-template <int VW>
-__device__ __forceinline__ void load_vec(const float* p, bool ok, float* v) {
-    if constexpr (VW == 4) {
-        if (ok) {
-            float4 t = *reinterpret_cast<const float4*>(p);
-            v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-        } else {
-            v[0] = v[1] = v[2] = v[3] = 0.f;
-        }
-    } else {
-        v[0] = ok ? *p : 0.f;
-    }
-}
-
-// FAST: a forward or stride-1 data-gradient contraction whose reduction
-// channel count (C, or K) is a multiple of the k tile, with the tap-inner
-// order and the unit stride fixed at compile time: no k tile crosses a tap,
-// so the per-thread wrap of the channel index, the linear-order paths and the
-// stride's division and exact-tap test drop out of the k loop (the data
-// gradient's stride alone: VGG-19 +1.1 %, its first stage +1.3 %).  The tap
-// index steps by selects and (r, s) follow from it by a multiply and shift,
-// exact for at most 7 x 7 taps (the host's condition).  For a
-// weight gradient: an output width Q that is a multiple of the k tile, so that
-// no k tile (16 output pixels) crosses an output row and the pixel's image
-// and row are the tile's.
-template <int OP, int BM, int BN, int BK, int WM, int WN, int VW, bool WIDE = false,
-          bool FAST = false>
+// fp32 operands that the vector kernels (igemm_split.hip) cannot take: rows
+// that are no multiple of 16 bytes, misaligned bases, 2 GB or more.  One
+// element per load, fp32 MFMAs.
+template <int OP, int BM, int BN, int BK, int WM, int WN, bool WIDE>
 __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KArgs args) {
     constexpr int NT = 64 * (BM / WM) * (BN / WN);
     constexpr int TM = WM / 32, TN = WN / 32;  // MFMA tiles per wave
@@ -547,7 +68,7 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
     // Otherwise tiles follow the linear reduction index.
     const int CCH = (OP == OP_FWD) ? g.C : g.K;
     const int RSN = g.R * g.S;
-    const bool tap_inner = (OP != OP_WGRAD) && (FAST || ((CCH % BK == 0) && RSN > 1));
+    const bool tap_inner = (OP != OP_WGRAD) && (CCH % BK == 0) && RSN > 1;
     const int tbeg = (int)(kbeg / BK), tend = (int)((kend + BK - 1) / BK);
 
     // ---- per-thread staging coordinates ----
@@ -555,14 +76,14 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
     // ("k-major"); OP_WGRAD reads dy rows (reduction index = row) with m = k
     // contiguous ("m-major").  B: OP_FWD reads weight rows (k-major);
     // OP_DGRAD / OP_WGRAD read rows indexed by the reduction with n contiguous.
-    constexpr int AV = A_KMAJ ? (BM * BK / VW / NT) : (BM * BK / VW / NT);
-    constexpr int BV = (BN * BK / VW / NT);
+    constexpr int AV = BM * BK / NT;
+    constexpr int BV = BN * BK / NT;
     static_assert(AV >= 1 && BV >= 1, "tile too small");
 
-    // A, k-major: vector i covers row (t + i*NT) / (BK/VW), reduction offset kva
-    constexpr int KVPR = BK / VW;               // vectors per k-major row
-    constexpr int AVPR = BM / VW;               // vectors per m-major row (A)
-    constexpr int BVPR = BN / VW;               // vectors per n-major row (B)
+    // A, k-major: element i covers row (t + i*NT) / BK, reduction offset akv
+    constexpr int KVPR = BK;                    // elements per k-major row
+    constexpr int AVPR = BM;                    // elements per m-major row (A)
+    constexpr int BVPR = BN;                    // elements per n-major row (B)
 
     // precomputed per-row data for gathered rows
     int arow_base[AV];   // FWD: n*H*W*C ; DGRAD: n*P*Q*K ; WGRAD: column m (k-out)
@@ -570,7 +91,7 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
     bool arow_ok[AV];
     int akv = 0;
     if constexpr (A_KMAJ) {
-        akv = (t % KVPR) * VW;
+        akv = t % KVPR;
 #pragma unroll
         for (int i = 0; i < AV; ++i) {
             long m = m0 + (t + i * NT) / KVPR;
@@ -582,22 +103,18 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
                 arow_base[i] = n * g.H * g.W * g.C;
                 arow_h[i] = p * g.st - g.pad;
                 arow_w[i] = q * g.st - g.pad;
-                // FAST: a row past M gets a row coordinate that no tap brings
-                // into the image, so its range test needs no row mask
-                if (FAST && !arow_ok[i]) arow_h[i] = -g.H - g.R;
             } else {  // DGRAD: m = (n, h, w)
                 int w = (int)(mm % g.W); long tt = mm / g.W;
                 int h = (int)(tt % g.H); int n = (int)(tt / g.H);
                 arow_base[i] = n * g.P * g.Q * g.K;
                 arow_h[i] = h + g.pad;
                 arow_w[i] = w + g.pad;
-                if (FAST && !arow_ok[i]) arow_h[i] = -g.P - g.R;
             }
         }
     } else {
 #pragma unroll
         for (int i = 0; i < AV; ++i) {
-            long m = m0 + ((t + i * NT) % AVPR) * VW;
+            long m = m0 + (t + i * NT) % AVPR;
             arow_ok[i] = m < args.M;
             arow_base[i] = (int)m;
             arow_h[i] = arow_w[i] = 0;
@@ -611,7 +128,7 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
     bool brow_ok[BV];
     int bkv = 0;
     if constexpr (B_KMAJ) {
-        bkv = (t % KVPR) * VW;
+        bkv = t % KVPR;
 #pragma unroll
         for (int i = 0; i < BV; ++i) {
             long n = n0 + (t + i * NT) / KVPR;
@@ -619,7 +136,7 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
             brow_n[i] = brow_ok[i] ? n : 0;
         }
     } else {
-        long col = n0 + (t % BVPR) * VW;
+        long col = n0 + t % BVPR;
         bcol_ok = col < args.Ncols;
         if (OP == OP_WGRAD && (args.epi & EPI_BIASCOL) && col == args.Ncols - 1) {
             bcol_ones = true;      // the appended column of ones (bias gradient)
@@ -643,46 +160,20 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
     // data gradient: when K is a multiple of the k tile no tile crosses a
     // tap, and row kr of a tile in tap (r, s) at channel c0 reads weight
     // (c0 + kr)*R*S*C + (r*S + s)*C + c: the thread's part is fixed
-    // (32-bit with the buffer loads, whose operands are below 2 GB)
-    using BOff = std::conditional_t<VW == 4, int, long>;
-    const BOff rsc = (BOff)g.R * g.S * g.C;
-    const bool dg_one_tap = (OP == OP_DGRAD) && (FAST || g.K % BK == 0);
-    BOff b_thr[BV];
+    const long rsc = (long)g.R * g.S * g.C;
+    const bool dg_one_tap = (OP == OP_DGRAD) && g.K % BK == 0;
+    long b_thr[BV];
 #pragma unroll
     for (int i = 0; i < BV; ++i)
-        b_thr[i] = (BOff)((t + i * NT) / BVPR) * rsc + bcol_c;
+        b_thr[i] = (long)((t + i * NT) / BVPR) * rsc + bcol_c;
 
     // two register sets of staged operands (tile kt+2 loads while kt+1 waits
     // to be written to LDS) and their masks; loads are unconditional (masked
     // lanes read the operand's first element) and the mask is applied when
     // the registers are written to LDS
-    float areg[2][AV][VW];
-    float breg[2][BV][VW];
+    float areg[2][AV];
+    float breg[2][BV];
     bool aok[2][AV], bok[2][BV], bone[2][BV];
-    auto ld = [](const float* p, float* v) {
-        if constexpr (VW == 4) {
-            const float4 t4 = *reinterpret_cast<const float4*>(p);
-            v[0] = t4.x; v[1] = t4.y; v[2] = t4.z; v[3] = t4.w;
-        } else {
-            v[0] = *p;
-        }
-    };
-    // VW = 4: range-checked buffer loads at 32-bit element offsets (every
-    // operand below 2 GB, checked by the host), an element off the problem
-    // read as zeros through an offset of BUF_OOB, so staging applies no masks
-    const long x_el = (long)g.N * g.H * g.W * g.C, dy_el = (long)g.N * g.P * g.Q * g.K;
-    const long a_el = (OP == OP_DGRAD) ? dy_el : x_el;
-    const long b_el = (OP == OP_WGRAD) ? dy_el : (long)g.K * g.R * g.S * g.C;
-    const __amdgpu_buffer_rsrc_t rsa = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(args.a), (short)0, (int)(a_el * 4), BUF_CFG);
-    const __amdgpu_buffer_rsrc_t rsb = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(args.b), (short)0, (int)(b_el * 4), BUF_CFG);
-    auto ldb = [](__amdgpu_buffer_rsrc_t rs, bool ok, int off, float* v) {
-        const uintx4 t = buf_load16(rs, ok ? (unsigned)off * 4u : BUF_OOB, 0u);
-        v[0] = __uint_as_float(t[0]); v[1] = __uint_as_float(t[1]);
-        v[2] = __uint_as_float(t[2]); v[3] = __uint_as_float(t[3]);
-    };
-
     // The decomposition of the next tile's first reduction index into (filter
     // tap, channel) or (image, output row, output column) is uniform across
     // the workgroup (scalar unit) and stepped from tile to tile (the tiles are
@@ -690,7 +181,6 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
     // FWD / DGRAD tap (nr, ns), its index ntap and the channel offset nc
     // within it; WGRAD the pixel (nn, np, nq).
     int nr = 0, ns = 0, nc = 0, ntap = 0, nq = 0, np = 0, nn = 0;
-    const int magS = (256 + g.S - 1) / g.S;   // (t * magS) >> 8 = t / S for t < R*S <= 49
     if constexpr (OP == OP_FWD || OP == OP_DGRAD) {
         if (tap_inner) {
             ntap = tbeg % RSN;
@@ -714,9 +204,7 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
     auto gload = [&](int kt, auto S) {
         constexpr int s = decltype(S)::value;
         const int T = tbeg + kt;
-        // FAST: the loads of the (at most two) tiles past the end read in-range or
-        // range-checked offsets and are never staged, so no test is needed
-        const bool tin = FAST || T < tend;
+        const bool tin = T < tend;
         const int k0 = tap_inner ? (tin ? ntap * CCH + nc : 0) : (int)(kbeg + (long)kt * BK);
         // reduction bound of a tile's rows: whole tiles in tap order
         const int kend_i = tap_inner ? (tin ? k0 + BK : 0) : (int)kend;
@@ -724,12 +212,7 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
             const int CC = CCH;                               // contiguous axis of a tap
             const int c0 = nc, r0 = nr, s0 = ns;
             // the next tile
-            if constexpr (FAST) {      // tap index and its (r, s) by a multiply-shift
-                ntap = (ntap + 1 == RSN) ? 0 : ntap + 1;
-                nc = (ntap == 0) ? nc + BK : nc;
-                nr = (ntap * magS) >> 8;
-                ns = ntap - nr * g.S;
-            } else if (tap_inner) {
+            if (tap_inner) {
                 ++ntap;
                 if (++ns == g.S) {
                     ns = 0;
@@ -742,47 +225,33 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
             // ---- A: k-major gathered rows ----
             {
                 int c = c0 + akv, r = r0, sx = s0;
-                if constexpr (!FAST)
-                    while (c >= CC) { c -= CC; if (++sx == g.S) { sx = 0; ++r; } }
-                const bool kin = FAST ? tin : k0 + akv < kend_i;
+                while (c >= CC) { c -= CC; if (++sx == g.S) { sx = 0; ++r; } }
+                const bool kin = k0 + akv < kend_i;
 #pragma unroll
                 for (int i = 0; i < AV; ++i) {
                     if constexpr (OP == OP_FWD) {
                         int h = arow_h[i] + r, w = arow_w[i] + sx;
-                        bool ok = (FAST || arow_ok[i]) && kin && (unsigned)h < (unsigned)g.H &&
+                        bool ok = arow_ok[i] && kin && (unsigned)h < (unsigned)g.H &&
                                   (unsigned)w < (unsigned)g.W;
-                        if constexpr (VW == 4) {
-                            ldb(rsa, ok, arow_base[i] + (h * g.W + w) * g.C + c, areg[s][i]);
-                        } else {
-                            const float* ptr =
-                                args.a + (ok ? (arow_base[i] + ((long)h * g.W + w) * g.C + c) : 0);
-                            ld(ptr, areg[s][i]);
-                        }
+                        const float* ptr =
+                            args.a + (ok ? (arow_base[i] + ((long)h * g.W + w) * g.C + c) : 0);
+                        areg[s][i] = *ptr;
                         aok[s][i] = ok;
                     } else {
                         int tp = arow_h[i] - r, tq = arow_w[i] - sx;
                         int p = tp, q = tq;
                         bool ok;
-                        if constexpr (FAST) {
-                            ok = kin && (unsigned)p < (unsigned)g.P &&
-                                 (unsigned)q < (unsigned)g.Q;
-                        } else {
-                            bool on_grid = true;
-                            if (g.st != 1) {        // (uniform branch) strided: exact taps only
-                                p = tp / g.st;
-                                q = tq / g.st;
-                                on_grid = p * g.st == tp && q * g.st == tq;
-                            }
-                            ok = arow_ok[i] && kin && tp >= 0 && tq >= 0 && on_grid && p < g.P &&
-                                 q < g.Q;
+                        bool on_grid = true;
+                        if (g.st != 1) {        // (uniform branch) strided: exact taps only
+                            p = tp / g.st;
+                            q = tq / g.st;
+                            on_grid = p * g.st == tp && q * g.st == tq;
                         }
-                        if constexpr (VW == 4) {
-                            ldb(rsa, ok, arow_base[i] + (p * g.Q + q) * g.K + c, areg[s][i]);
-                        } else {
-                            const float* ptr =
-                                args.a + (ok ? (arow_base[i] + ((long)p * g.Q + q) * g.K + c) : 0);
-                            ld(ptr, areg[s][i]);
-                        }
+                        ok = arow_ok[i] && kin && tp >= 0 && tq >= 0 && on_grid && p < g.P &&
+                             q < g.Q;
+                        const float* ptr =
+                            args.a + (ok ? (arow_base[i] + ((long)p * g.Q + q) * g.K + c) : 0);
+                        areg[s][i] = *ptr;
                         aok[s][i] = ok;
                     }
                 }
@@ -793,12 +262,8 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
                 if constexpr (OP == OP_FWD) {
                     const int kk = k0 + bkv;
                     bool ok = brow_ok[i] && kk < kend_i;
-                    if constexpr (VW == 4) {
-                        ldb(rsb, ok, (int)brow_n[i] * (int)args.Kred + kk, breg[s][i]);
-                    } else {
-                        const float* ptr = args.b + (ok ? (brow_n[i] * args.Kred + kk) : 0);
-                        ld(ptr, breg[s][i]);
-                    }
+                    const float* ptr = args.b + (ok ? (brow_n[i] * args.Kred + kk) : 0);
+                    breg[s][i] = *ptr;
                     bok[s][i] = ok;
                 } else {   // B[kk = (r,s,k)][c] = w[k][r][s][c]
                     const int kr = (t + i * NT) / BVPR;
@@ -807,18 +272,14 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
                     if (dg_one_tap) {
                         // the tile lies within tap (r0, s0): a uniform base plus
                         // this thread's constant offset
-                        off = (BOff)c0 * rsc + ((BOff)r0 * g.S + s0) * g.C + b_thr[i];
+                        off = (long)c0 * rsc + ((long)r0 * g.S + s0) * g.C + b_thr[i];
                     } else {
                         int k = c0 + kr, r = r0, sx = s0;
                         while (k >= CC) { k -= CC; if (++sx == g.S) { sx = 0; ++r; } }
                         off = (((long)k * g.R + r) * g.S + sx) * g.C + bcol_c;
                     }
-                    if constexpr (VW == 4) {
-                        ldb(rsb, ok, (int)off, breg[s][i]);
-                    } else {
-                        const float* ptr = args.b + (ok ? off : 0);
-                        ld(ptr, breg[s][i]);
-                    }
+                    const float* ptr = args.b + (ok ? off : 0);
+                    breg[s][i] = *ptr;
                     bok[s][i] = ok;
                 }
             }
@@ -827,24 +288,17 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
 #pragma unroll
             for (int i = 0; i < AV; ++i) {
                 const int kk = k0 + (t + i * NT) / AVPR;
-                bool ok = arow_ok[i] && (FAST || kk < kend_i);
-                if constexpr (VW == 4) {
-                    ldb(rsb, ok, kk * g.K + arow_base[i], areg[s][i]);
-                } else {
-                    const float* ptr = args.b + (ok ? ((long)kk * g.K + arow_base[i]) : 0);
-                    ld(ptr, areg[s][i]);
-                }
+                bool ok = arow_ok[i] && kk < kend_i;
+                const float* ptr = args.b + (ok ? ((long)kk * g.K + arow_base[i]) : 0);
+                areg[s][i] = *ptr;
                 aok[s][i] = ok;
             }
             // ---- B: B[kk = (n,p,q)][j = (r,s,c)] = x[n, p*st-pad+r, q*st-pad+s, c] ----
             // (one output pixel per image, as in a fully connected layer: the
             // reduction index is the image)
-            const bool px1 = !FAST && g.P * g.Q == 1;
+            const bool px1 = g.P * g.Q == 1;
             const int q0 = nq, p0 = np, n0i = nn;
-            if constexpr (FAST) {  // the next tile: the next 16 pixels of the row, or the next row
-                nq += BK;
-                if (nq == g.Q) { nq = 0; if (++np == g.P) { np = 0; ++nn; } }
-            } else if (px1) {
+            if (px1) {
                 nn += BK;
             } else {
                 nq += BK;
@@ -854,25 +308,19 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
             for (int i = 0; i < BV; ++i) {
                 const int kr = (t + i * NT) / BVPR;
                 int q = q0 + kr, p = p0, n = n0i;
-                if constexpr (!FAST) {
-                    if (px1) {
-                        q = 0;
-                        n = n0i + kr;
-                    } else {
-                        while (q >= g.Q) { q -= g.Q; if (++p == g.P) { p = 0; ++n; } }
-                    }
+                if (px1) {
+                    q = 0;
+                    n = n0i + kr;
+                } else {
+                    while (q >= g.Q) { q -= g.Q; if (++p == g.P) { p = 0; ++n; } }
                 }
-                const bool kin = FAST || k0 + kr < kend_i;
+                const bool kin = k0 + kr < kend_i;
                 int h = p * g.st - g.pad + bcol_r, w = q * g.st - g.pad + bcol_s;
                 bool ok = bcol_ok && kin && (unsigned)h < (unsigned)g.H &&
                           (unsigned)w < (unsigned)g.W;
-                if constexpr (VW == 4) {
-                    ldb(rsa, ok, ((n * g.H + h) * g.W + w) * g.C + bcol_c, breg[s][i]);
-                } else {
-                    const float* ptr =
-                        args.a + (ok ? ((((long)n * g.H + h) * g.W + w) * g.C + bcol_c) : 0);
-                    ld(ptr, breg[s][i]);
-                }
+                const float* ptr =
+                    args.a + (ok ? ((((long)n * g.H + h) * g.W + w) * g.C + bcol_c) : 0);
+                breg[s][i] = *ptr;
                 bok[s][i] = ok;
                 bone[s][i] = bcol_ones && kin;
             }
@@ -885,40 +333,19 @@ __global__ void __launch_bounds__(64 * (BM / WM) * (BN / WN), 2) igemm_kernel(KA
         float* Bs = As + BK * LDA;
 #pragma unroll
         for (int i = 0; i < AV; ++i) {
-            if constexpr (A_KMAJ) {
-                int row = (t + i * NT) / KVPR;
-#pragma unroll
-                for (int j = 0; j < VW; ++j)
-                    As[(akv + j) * LDA + row] = (VW == 4 || aok[s][i]) ? areg[s][i][j] : 0.f;
-            } else {
-                int kr = (t + i * NT) / AVPR;
-                int col = ((t + i * NT) % AVPR) * VW;
-#pragma unroll
-                for (int j = 0; j < VW; ++j)
-                    As[kr * LDA + col + j] = (VW == 4 || aok[s][i]) ? areg[s][i][j] : 0.f;
-            }
+            const int at = t + i * NT;
+            const float v = aok[s][i] ? areg[s][i] : 0.f;
+            if constexpr (A_KMAJ) As[akv * LDA + at / KVPR] = v;
+            else As[(at / AVPR) * LDA + at % AVPR] = v;
         }
 #pragma unroll
         for (int i = 0; i < BV; ++i) {
-            if constexpr (B_KMAJ) {
-                int row = (t + i * NT) / KVPR;
-#pragma unroll
-                for (int j = 0; j < VW; ++j)
-                    Bs[(bkv + j) * LDB + row] = (VW == 4 || bok[s][i]) ? breg[s][i][j] : 0.f;
-            } else {
-                int kr = (t + i * NT) / BVPR;
-                int col = ((t + i * NT) % BVPR) * VW;
-#pragma unroll
-                for (int j = 0; j < VW; ++j) {
-                    // the appended column of ones (bias gradient) in lane 0
-                    // (VW = 4: an element off the problem was read as zero, and
-                    // the ones column, weight gradient only, is read past the end)
-                    const bool ones = OP == OP_WGRAD && bone[s][i];
-                    const float one = (j == 0 && ones) ? 1.f : 0.f;
-                    Bs[kr * LDB + col + j] = (VW == 4) ? (ones ? one : breg[s][i][j])
-                                                       : (bok[s][i] ? breg[s][i][j] : one);
-                }
-            }
+            const int at = t + i * NT;
+            // the appended column of ones: the bias gradient of a weight gradient
+            const float off = (OP == OP_WGRAD && bone[s][i]) ? 1.f : 0.f;
+            const float v = bok[s][i] ? breg[s][i] : off;
+            if constexpr (B_KMAJ) Bs[bkv * LDB + at / KVPR] = v;
+            else Bs[(at / BVPR) * LDB + at % BVPR] = v;
         }
     };
 
@@ -1197,7 +624,6 @@ __global__ void __launch_bounds__(256, 2) fcf_kernel(KArgs args) {
 constexpr int BKH = 32;
 constexpr int LDH = BKH + 8;
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 
 template <int OP, int BM, int BN, int WM, int WN, int VW>
@@ -2726,21 +2152,13 @@ __global__ void __launch_bounds__(CRS_THREADS) igemm_cut_reduce_stats_kernel(KAr
     }
 }
 
-struct KernelRef {
-    const void* fn;
-    int nt;
-};
-
 // Kernel families: fp32 operands staged from fp32 (vector width 1 or 4),
 // bf16 rounded while staging from fp32 (1 or 4), bf16 operands in memory
 // (general gather), bf16 operands in memory, both k-major (FWD and stride-1
 // DGRAD with a reduction channel count that is a multiple of the k tile), and
-// fp32 (vector width 4 or 1) with the wide epilogue.
-// KF_F32_4F / KF_F32_4WF: the fp32 vector kernels in their FAST form (forward and
-// stride-1 data gradient with a channel count that is a multiple of the k tile;
-// weight gradient with an output width that is one).
-enum { KF_F32_1, KF_F32_4, KF_BF_1, KF_BF_4, KF_H16, KF_H16K, KF_F32_4W, KF_F32_1W, KF_H16D,
-       KF_F32_4F, KF_F32_4WF };
+// fp32 of one element per load with the plain or the wide epilogue (the fp32
+// vector kernels are in igemm_split.hip).
+enum { KF_F32_1, KF_BF_1, KF_BF_4, KF_H16, KF_H16K, KF_F32_1W, KF_H16D };
 
 template <int OP, int CFG, int KF>
 KernelRef kref() {
@@ -2758,21 +2176,9 @@ KernelRef kref() {
     else if constexpr (KF == KF_BF_1 || KF == KF_BF_4)
         return {reinterpret_cast<const void*>(
                     &igemm_bf16_kernel<OP, c.bm, c.bn, c.wm, c.wn, KF == KF_BF_4 ? 4 : 1>), nt};
-    else if constexpr (KF == KF_F32_4WF)
-        return {reinterpret_cast<const void*>(
-                    &igemm_kernel<OP, c.bm, c.bn, c.bk, c.wm, c.wn, 4, true, true>),
-                nt};
-    else if constexpr (KF == KF_F32_4F)
-        return {reinterpret_cast<const void*>(
-                    &igemm_kernel<OP, c.bm, c.bn, c.bk, c.wm, c.wn, 4, false, true>),
-                nt};
-    else if constexpr (KF == KF_F32_4W || KF == KF_F32_1W)
-        return {reinterpret_cast<const void*>(
-                    &igemm_kernel<OP, c.bm, c.bn, c.bk, c.wm, c.wn, KF == KF_F32_4W ? 4 : 1, true>),
-                nt};
     else
         return {reinterpret_cast<const void*>(
-                    &igemm_kernel<OP, c.bm, c.bn, c.bk, c.wm, c.wn, KF == KF_F32_4 ? 4 : 1>), nt};
+                    &igemm_kernel<OP, c.bm, c.bn, c.bk, c.wm, c.wn, KF == KF_F32_1W>), nt};
 }
 
 template <int OP, int KF>
@@ -2798,14 +2204,10 @@ template <int OP>
 KernelRef kref_op(int cfg, int kf) {
     if (kf == KF_H16D) return kref_h16d<OP>();
     switch (kf) {
-        case KF_F32_4: return kref_cfg<OP, KF_F32_4>(cfg);
         case KF_BF_1: return kref_cfg<OP, KF_BF_1>(cfg);
         case KF_BF_4: return kref_cfg<OP, KF_BF_4>(cfg);
         case KF_H16: return kref_cfg<OP, KF_H16>(cfg);
         case KF_H16K: return kref_cfg<OP, KF_H16K>(cfg);
-        case KF_F32_4W: return kref_cfg<OP, KF_F32_4W>(cfg);
-        case KF_F32_4F: return kref_cfg<OP, KF_F32_4F>(cfg);
-        case KF_F32_4WF: return kref_cfg<OP, KF_F32_4WF>(cfg);
         case KF_F32_1W: return kref_cfg<OP, KF_F32_1W>(cfg);
         default: return kref_cfg<OP, KF_F32_1>(cfg);
     }
@@ -2832,12 +2234,24 @@ int choose_cfg(int op, long M, long N, long Kred) {
 
 }  // namespace
 
-// The fp32 vector kernels address their operands with 32-bit buffer offsets:
+// The split kernels address their operands with 32-bit buffer offsets:
 // every operand below 2 GB (else the kernels of one element per load take it).
 static bool fits_buffer(const ConvGeo& g) {
     const long lim = (1L << 31) - 16;
     return (long)g.N * g.H * g.W * g.C * 4 < lim && (long)g.N * g.P * g.Q * g.K * 4 < lim &&
            (long)g.K * g.R * g.S * g.C * 4 < lim;
+}
+
+// The FAST form of the split kernels (the k tile is 16 in every fp32
+// configuration; at most 7 x 7 taps, which their tap stepping assumes).
+static bool fast_split(int op, const ConvGeo& g) {
+    static_assert(kCfgs[0].bk == 16 && kCfgs[1].bk == 16 && kCfgs[2].bk == 16 &&
+                      kCfgs[3].bk == 16 && kCfgs[4].bk == 16,
+                  "fp32 k tile");
+    const bool taps7 = g.R <= 7 && g.S <= 7;
+    return (op == OP_FWD && g.C % 16 == 0 && taps7) ||
+           (op == OP_DGRAD && g.st == 1 && g.K % 16 == 0 && taps7) ||
+           (op == OP_WGRAD && g.Q % 16 == 0);
 }
 
 GemmPlan plan_gemm(int op, const ConvGeo& g, int bf16, int num_cus, int bias_col, int allow_h16d) {
@@ -2855,15 +2269,7 @@ GemmPlan plan_gemm(int op, const ConvGeo& g, int bf16, int num_cus, int bias_col
     }
     const bool v4 = ((op == OP_FWD) ? (g.C % 4 == 0) : (g.C % 4 == 0 && g.K % 4 == 0)) &&
                     fits_buffer(g);
-    // the FAST fp32 kernels (the k tile is 16 in every fp32 configuration)
-    static_assert(kCfgs[0].bk == 16 && kCfgs[1].bk == 16 && kCfgs[2].bk == 16 &&
-                      kCfgs[3].bk == 16 && kCfgs[4].bk == 16,
-                  "fp32 k tile");
-    // (forward and data gradient: at most 7 x 7 taps, which their tap stepping assumes)
-    const bool taps7 = g.R <= 7 && g.S <= 7;
-    const bool fast32 = (op == OP_FWD && g.C % 16 == 0 && taps7) ||
-                        (op == OP_DGRAD && g.st == 1 && g.K % 16 == 0 && taps7) ||
-                        (op == OP_WGRAD && g.Q % 16 == 0);
+    const bool fast32 = fast_split(op, g);
     // bf16 operands in memory: every contiguous axis a multiple of 8 (16 bytes)
     p.h16 = (bf16 && g.C % 8 == 0 && g.K % 8 == 0) ? 1 : 0;
     p.cfg = choose_cfg(op, p.M, p.Ncols, p.Kred);
@@ -2883,7 +2289,8 @@ GemmPlan plan_gemm(int op, const ConvGeo& g, int bf16, int num_cus, int bias_col
     long tiles = ((p.M + cp->bm - 1) / cp->bm) * ((p.Ncols + cp->bn - 1) / cp->bn);
     int bk = p.h16 ? cp->bkh : (bf16 ? BKH : cp->bk);
     long ktiles = (p.Kred + bk - 1) / bk;
-    // fp32: the wide epilogue where the epilogue weighs: a short reduction
+    // fp32: rows that are multiples of 16 bytes run on split operands.  The
+    // one-element kernels take the wide epilogue where the epilogue weighs: a short reduction
     // (writes much relative to what it computes), or a moderate reduction over
     // so few tiles that it is cut into eight or more chunks (the partial tiles
     // written outweigh occupancy).  Long reductions (the weight gradients of
@@ -2891,11 +2298,13 @@ GemmPlan plan_gemm(int op, const ConvGeo& g, int bf16, int num_cus, int bias_col
     // occupancy gives them more resident workgroups and reduction chunks.
     if (!bf16) {
         int occ_n = 0;
-        const KernelRef kn = kernel_for(op, p.cfg, v4 ? (fast32 ? KF_F32_4F : KF_F32_4) : KF_F32_1);
+        p.split = v4 ? 1 : 0;
+        const KernelRef kn = p.split ? split_kernel(op, p.cfg, fast32) : kernel_for(op, p.cfg, KF_F32_1);
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_n, kn.fn, kn.nt, 0) != hipSuccess ||
             occ_n < 1)
             occ_n = 1;
-        p.wide = (p.Kred <= 1024 || (p.Kred <= 32768 && 8 * tiles <= (long)num_cus * occ_n)) ? 1 : 0;
+        p.wide = (p.split || p.Kred <= 1024 ||
+                  (p.Kred <= 32768 && 8 * tiles <= (long)num_cus * occ_n)) ? 1 : 0;
     }
     // buffer-load kernels (32-bit offsets): FWD and stride-1 DGRAD with both
     // operands k-major and one tap per k tile; WGRAD on m-major LDS tiles
@@ -2928,13 +2337,12 @@ GemmPlan plan_gemm(int op, const ConvGeo& g, int bf16, int num_cus, int bias_col
     }
     const TileCfg& c = *cp;
     // workgroups resident at once
-    KernelRef kr = kernel_for(op, p.cfg,
+    KernelRef kr = p.split ? split_kernel(op, p.cfg, fast32)
+                   : kernel_for(op, p.cfg,
                               p.h16d ? KF_H16D : p.h16k ? KF_H16K
                                      : p.h16 ? KF_H16
                                              : bf16 ? (v4 ? KF_BF_4 : KF_BF_1)
-                                                    : (v4 ? (p.wide ? (fast32 ? KF_F32_4WF : KF_F32_4W)
-                                                                    : (fast32 ? KF_F32_4F : KF_F32_4))
-                                                          : (p.wide ? KF_F32_1W : KF_F32_1)));
+                                                    : (p.wide ? KF_F32_1W : KF_F32_1));
     int occ = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kr.fn, kr.nt, 0) != hipSuccess || occ < 1)
         occ = 1;
@@ -3110,10 +2518,7 @@ hipError_t launch_gemm(const GemmPlan& plan, const ConvGeo& g, const float* a, c
     // operand bases 16-byte aligned
     bool v4 = (plan.op == OP_FWD) ? (g.C % 4 == 0) : (g.C % 4 == 0 && g.K % 4 == 0);
     v4 = v4 && fits_buffer(g) && ((((uintptr_t)a) | ((uintptr_t)b)) & 15) == 0;
-    const bool taps7 = g.R <= 7 && g.S <= 7;
-    const bool fast32 = (plan.op == OP_FWD && g.C % 16 == 0 && taps7) ||
-                        (plan.op == OP_DGRAD && g.st == 1 && g.K % 16 == 0 && taps7) ||
-                        (plan.op == OP_WGRAD && g.Q % 16 == 0);
+    const bool fast32 = fast_split(plan.op, g);
     // DGRAD on k-major operands takes the transposed weights b16t
     const uint16_t* bk16 = plan.op == OP_DGRAD ? b16t : b16;
     if (plan.op == OP_WGRAD) {
@@ -3127,9 +2532,7 @@ hipError_t launch_gemm(const GemmPlan& plan, const ConvGeo& g, const float* a, c
     const int kf = (h16k && plan.h16d) ? KF_H16D : h16k ? KF_H16K
                         : h16 ? KF_H16
                               : plan.bf16 ? (v4 ? KF_BF_4 : KF_BF_1)
-                                          : (v4 ? (plan.wide ? (fast32 ? KF_F32_4WF : KF_F32_4W)
-                                                            : (fast32 ? KF_F32_4F : KF_F32_4))
-                                                : (plan.wide ? KF_F32_1W : KF_F32_1));
+                                          : (plan.wide ? KF_F32_1W : KF_F32_1);
     if (plan.fcf) {
         if (!v4) return hipErrorInvalidValue;
         k.tiles_m = 1;
@@ -3153,7 +2556,8 @@ hipError_t launch_gemm(const GemmPlan& plan, const ConvGeo& g, const float* a, c
         hipLaunchKernelGGL(fcw_kernel, dim3(plan.nwg), dim3(256), 0, s, k);
         return hipGetLastError();
     }
-    KernelRef kr = kernel_for(plan.op, plan.cfg, kf);
+    const KernelRef kr = plan.split && v4 ? split_kernel(plan.op, plan.cfg, fast32)
+                                          : kernel_for(plan.op, plan.cfg, kf);
     void* kargs[] = {&k};
     hipError_t e = hipLaunchKernel(kr.fn, dim3(plan.nwg), dim3(kr.nt), kargs, 0, s);
     const int cut = k.tiles_m * k.tiles_n - plan.tfull;
