@@ -17,7 +17,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libhetpipe.so")
-SOURCES = ["igemm.hip", "igemm_split.hip", "elementwise.hip", "wsp.hip", "hetpipe.cpp"]
+SOURCES = ["igemm.hip", "igemm_split.hip", "igemm_planes.hip",
+           "elementwise.hip", "wsp.hip", "hetpipe.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
@@ -34,6 +35,7 @@ EXTRA = {"wsp.hip": ["-ffp-contract=off"]}
 
 
 HEADERS = [os.path.join(CSRC, "kernels.h"), os.path.join(CSRC, "igemm_common.h"),
+           os.path.join(CSRC, "igemm_pieces.h"),
            os.path.join(ROOT, "include", "hetpipe.h")]
 
 

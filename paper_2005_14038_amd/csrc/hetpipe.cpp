@@ -84,6 +84,18 @@ struct Node {
     // the BN backward that produces it, else cast before the weight gradient)
     uint16_t* g16 = nullptr;
     bool g16_ready = false;
+    // fp32 contractions on operands split in memory (plan.planes): the planes of
+    // this node's output (made by its first such consumer in the forward pass,
+    // kept for the weight gradient) and of its output gradient, and the place of
+    // its weights within the stage's weight planes
+    uint16_t* y3 = nullptr;
+    bool y3_ready = false;
+    uint16_t* g3 = nullptr;
+    long w3_off = 0;
+    int w3_at = 0;
+    bool x_planes() const { return fwd.planes || wgrad.planes; }
+    bool g_planes() const { return dgrad.planes || wgrad.planes; }
+    bool w_planes() const { return fwd.planes || dgrad.planes; }
     // max-pool with overlapping windows: the tap of each window's first
     // maximum, recorded by the forward pass for the backward pass
     uint8_t* arg = nullptr;
@@ -107,6 +119,11 @@ struct Node {
 };
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+
+// a workspace's share of the static scratch
+size_t workspace_bytes(size_t floats) {
+    return round_up(std::max<size_t>(floats, 64) * sizeof(float), 256);
+}
 
 }  // namespace
 
@@ -180,6 +197,22 @@ struct hp_stage {
     int wt_layers = 0, wt_tiles_total = 0;
     uint16_t* x16 = nullptr;
     bool x16_ready = false;
+    // fp32: planes of the stage input, and of the weights of the layers that
+    // read them, in their own order and transposed ([C][R][S][K])
+    uint16_t* x3 = nullptr;
+    bool x3_ready = false;
+    uint16_t* w3 = nullptr;
+    uint16_t* w3t = nullptr;
+    long w3_plane = 0;
+    // largest magnitudes, cleared by the forward pass: stage input, outputs,
+    // output gradients, then the layers of w3_table
+    unsigned* amax = nullptr;
+    unsigned* amax_y(int j) { return amax + 1 + j; }       // j = -1: the stage input
+    unsigned* amax_g(int j) { return amax + 1 + nodes.size() + j; }
+    unsigned* amax_w(int at) { return amax + 1 + 2 * nodes.size() + at; }
+    int amax_count() const { return 1 + 2 * (int)nodes.size() + w3_layers; }
+    WpLayer* w3_table = nullptr;
+    int w3_layers = 0, w3_tiles = 0;
     // the weight gradients run on a second stream beside the data-gradient
     // chain (they only feed the caller's gradient vector), with a workspace
     // of their own; events order the two streams
@@ -258,6 +291,41 @@ int num_cus() {
     if (hipGetDevice(&dev) == hipSuccess)
         (void)hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
     return n > 0 ? n : 256;
+}
+
+// fp32 convolutions move to the kernels on operands split in memory where
+// plan_gemm has such a plan, except
+// - a forward whose column statistics a batch norm reads (those kernels'
+//   epilogue forms none), and
+// - a plan whose partial tiles would take the stage's workspaces past the static
+//   scratch that hp_stage_backward_noalloc has for them: what that call took
+//   without these plans it takes with them.
+// Their weight gradients fill the GPU and stay in stream order.
+void plan_planes(hp_stage* st) {
+    const int cus = num_cus();
+    const size_t taken = workspace_bytes(st->ws2_floats);
+    if (taken >= HP_NOALLOC_SCRATCH_BYTES) return;
+    const long room = (long)((HP_NOALLOC_SCRATCH_BYTES - taken) / sizeof(float));
+    for (size_t i = 0; i < st->nodes.size(); ++i) {
+        Node& nd = st->nodes[i];
+        if (nd.L.kind != HP_CONV || nd.padC) continue;
+        bool bn = false;
+        for (const Node& c : st->nodes) bn |= c.L.kind == HP_BN && c.L.in0 == (int)i;
+        auto take = [&](GemmPlan& p, int op, size_t more) {
+            const GemmPlan q = plan_gemm(op, nd.geo, HP_FP32, cus, 0, 1, room);
+            const size_t ws = std::max({st->ws_floats, q.ws_floats, more});
+            if (!q.planes || workspace_bytes(ws) + workspace_bytes(st->ws2_floats) >
+                                 HP_NOALLOC_SCRATCH_BYTES)
+                return;
+            p = q;
+            st->ws_floats = ws;
+        };
+        if (!bn) take(nd.fwd, OP_FWD, 0);
+        take(nd.dgrad, OP_DGRAD, 0);
+        take(nd.wgrad, OP_WGRAD,
+             nd.L.bias ? colsum_ws_floats((long)st->batch * nd.H * nd.W, nd.C) : 0);
+        if (nd.wgrad.planes) nd.bias_in_wgrad = nd.wgrad_side = false;
+    }
 }
 
 int shape_of(const hp_stage* st, int idx, int& H, int& W, int& C) {
@@ -443,6 +511,7 @@ int build_stage(hp_stage* st, const hp_layer* layers, int n_layers) {
         nd.mask_into = r.L.in0;
         r.bwd_by_consumer = true;
     }
+    if (st->dtype == HP_FP32) plan_planes(st);
     // device buffers
     st->node_bytes.assign(n_layers, 0);
     for (int i = 0; i < n_layers; ++i) {
@@ -536,6 +605,54 @@ int build_stage(hp_stage* st, const hp_layer* layers, int n_layers) {
             st->wt_layers = (int)tab.size();
             st->wt_tiles_total = tiles;
         }
+    }
+    // planes of the fp32 contractions that read operands split in memory
+    std::vector<WpLayer> ptab;
+    int ptiles = 0;
+    for (int i = 0; i < n_layers; ++i) {
+        Node& nd = st->nodes[i];
+        if (nd.L.kind != HP_CONV) continue;
+        int rc = HP_OK;
+        st->cur_node = i;
+        if (nd.g_planes()) rc = dev_alloc16(st, &nd.g3, 2 * nd.out_elems);
+        const int j = nd.L.in0;
+        st->cur_node = j;
+        if (!rc && nd.x_planes()) {
+            const size_t n_in = (size_t)st->batch * nd.inH * nd.inW * nd.inC;
+            uint16_t*& at = j < 0 ? st->x3 : st->nodes[j].y3;
+            if (!at) rc = dev_alloc16(st, &at, 2 * n_in);
+        }
+        if (rc) return rc;
+        if (nd.w_planes()) {
+            const ConvGeo& g = nd.geo;
+            nd.w3_off = st->w3_plane;
+            nd.w3_at = (int)ptab.size();
+            ptab.push_back(WpLayer{(long)nd.w_off, nd.w3_off, g.K, g.R * g.S, g.C, ptiles});
+            ptiles += wt_tiles(g.K, g.R * g.S, g.C);
+            // every layer starts on 16 bytes
+            st->w3_plane += (long)round_up((size_t)g.K * g.R * g.S * g.C, 8);
+        }
+    }
+    st->cur_node = -1;
+    if (!ptab.empty()) {
+        int rc = dev_alloc16(st, &st->w3, 2 * (size_t)st->w3_plane);
+        if (!rc) rc = dev_alloc16(st, &st->w3t, 2 * (size_t)st->w3_plane);
+        float* t = nullptr;
+        const size_t tb = ptab.size() * sizeof(WpLayer);
+        if (!rc) rc = dev_alloc(st, &t, (tb + 3) / 4);
+        if (rc) return rc;
+        HP_HIP(hipMemcpy(t, ptab.data(), tb, hipMemcpyHostToDevice));
+        st->w3_table = reinterpret_cast<WpLayer*>(t);
+        st->w3_layers = (int)ptab.size();
+        st->w3_tiles = ptiles;
+    }
+    bool any3 = st->w3 != nullptr;
+    for (const Node& nd : st->nodes) any3 |= nd.g3 != nullptr;
+    if (any3) {
+        float* m = nullptr;
+        int rc = dev_alloc(st, &m, (size_t)st->amax_count());
+        if (rc) return rc;
+        st->amax = reinterpret_cast<unsigned*>(m);
     }
     int rc = dev_alloc(st, &st->ws2, std::max<size_t>(st->ws2_floats, 64));
     if (rc) return rc;
@@ -695,7 +812,8 @@ extern "C" int hp_stage_forward(hp_stage* st, const float* w, const float* x, fl
     hipStream_t s = st->stream;
     const int B = st->batch;
     st->x16_ready = false;
-    for (Node& nd : st->nodes) nd.y16_ready = false;
+    st->x3_ready = false;
+    for (Node& nd : st->nodes) nd.y16_ready = nd.y3_ready = false;
     st->timer.node = -1;
     st->timer.phase = 0;
     if (st->w16) {
@@ -708,6 +826,16 @@ extern "C" int hp_stage_forward(hp_stage* st, const float* w, const float* x, fl
         int rc = launch_ok(e, "weight cast", -1);
         if (rc) return rc;
     }
+    if (st->amax) {
+        st->timer.begin(1, s);
+        hipError_t e = launch_clear(st->amax, st->amax_count(), s);
+        if (e == hipSuccess)
+            e = launch_split_weights(w, st->w3, st->w3t, st->w3_plane, st->w3_table,
+                                     st->w3_layers, st->w3_tiles, st->amax_w(0), s);
+        st->timer.end(s);
+        int rc = launch_ok(e, "weight split", -1);
+        if (rc) return rc;
+    }
     for (size_t i = 0; i < st->nodes.size(); ++i) {
         Node& nd = st->nodes[i];
         const hp_layer& L = nd.L;
@@ -715,6 +843,21 @@ extern "C" int hp_stage_forward(hp_stage* st, const float* w, const float* x, fl
         st->timer.node = (int)i;
         hipError_t e = hipSuccess;
         StageTimer& tm = st->timer;
+        const uint16_t* in3 = nullptr;
+        if (L.kind == HP_CONV && nd.x_planes()) {
+            uint16_t* p3 = L.in0 < 0 ? st->x3 : st->nodes[L.in0].y3;
+            bool& ready = L.in0 < 0 ? st->x3_ready : st->nodes[L.in0].y3_ready;
+            if (!ready) {
+                tm.begin(1, s);
+                e = launch_split_planes(in, p3, (size_t)B * nd.inH * nd.inW * nd.inC,
+                                        st->amax_y(L.in0), s);
+                tm.end(s);
+                int rc = launch_ok(e, "activation split", (int)i);
+                if (rc) return rc;
+                ready = true;
+            }
+            in3 = p3;
+        }
         const uint16_t* in16 = nullptr;
         if ((L.kind == HP_CONV || L.kind == HP_FC) && nd.fwd.h16 && st->w16 && !nd.padC) {
             // bf16 copy of the input value, made by its first contraction consumer
@@ -770,6 +913,12 @@ extern "C" int hp_stage_forward(hp_stage* st, const float* w, const float* x, fl
                     if (e == hipSuccess)
                         e = launch_gemm(nd.fwd, nd.geo_p, nd.xp ? nd.xp : in, nd.wp ? nd.wp : w,
                                         nd.y, ep, st->ws, s, nd.xp16, nd.wp16);
+                    break;
+                }
+                if (nd.fwd.planes) {
+                    const Planes pl{st->w3_plane, st->amax_y(L.in0), st->amax_w(nd.w3_at)};
+                    e = launch_gemm(nd.fwd, nd.geo, in, w + nd.w_off, nd.y, ep, st->ws, s, in3,
+                                    st->w3 + nd.w3_off, nullptr, &pl);
                     break;
                 }
                 e = launch_gemm(nd.fwd, nd.geo, in, w + nd.w_off, nd.y, ep, st->ws, s, in16,
@@ -929,6 +1078,15 @@ int stage_backward(hp_stage* st, const float* w, const float* dy, float* dx, flo
                     }
                     g16 = nd.g16;
                 }
+                if (nd.g_planes()) {
+                    tm.begin(1, s);
+                    e = launch_split_planes(gin, nd.g3, nd.out_elems, st->amax_g(i), s);
+                    tm.end(s);
+                }
+                if (nd.wgrad.planes) {
+                    in16 = L.in0 < 0 ? st->x3 : st->nodes[L.in0].y3;
+                    g16 = nd.g3;
+                }
                 // weight gradient (and a separate bias column sum), on the side
                 // stream once gin and its bf16 copy are complete
                 hipStream_t sd = nd.wgrad_side ? st->side : s;
@@ -945,8 +1103,10 @@ int stage_backward(hp_stage* st, const float* w, const float* dy, float* dx, flo
                         e = launch_unpad_channels(nd.dwp, grad + nd.w_off,
                                                   (size_t)L.K * L.R * L.S, nd.geo.C, nd.padC, sd);
                 } else if (e == hipSuccess) {
+                    const Planes pl{0, nd.wgrad.planes ? st->amax_y(L.in0) : nullptr,
+                                    nd.wgrad.planes ? st->amax_g(i) : nullptr};
                     e = launch_gemm(nd.wgrad, nd.geo, in, gin, grad + nd.w_off, wep, wsw, sd,
-                                    in16, g16);
+                                    in16, g16, nullptr, &pl);
                 }
                 tm.end(sd);
                 if (e == hipSuccess && L.bias && !nd.bias_in_wgrad) {
@@ -964,9 +1124,16 @@ int stage_backward(hp_stage* st, const float* w, const float* dy, float* dx, flo
                     }
                     dep.out16 = sole_grad16(tgt, acc);
                     tm.begin(0, s);
-                    e = launch_gemm(nd.dgrad, nd.geo, gin, w + nd.w_off, d, dep, ws, s, g16,
-                                    g16 ? st->w16 + nd.w_off : nullptr,
-                                    g16 && st->w16t ? st->w16t + nd.w_off : nullptr);
+                    if (nd.dgrad.planes) {
+                        const Planes pl{st->w3_plane, st->amax_g(i), st->amax_w(nd.w3_at)};
+                        e = launch_gemm(nd.dgrad, nd.geo, gin, w + nd.w_off, d, dep, ws, s, nd.g3,
+                                        nullptr, st->w3t + nd.w3_off, &pl);
+                    } else if (st->w16 && g16)
+                        e = launch_gemm(nd.dgrad, nd.geo, gin, w + nd.w_off, d, dep, ws, s, g16,
+                                        st->w16 + nd.w_off,
+                                        st->w16t ? st->w16t + nd.w_off : nullptr);
+                    else
+                        e = launch_gemm(nd.dgrad, nd.geo, gin, w + nd.w_off, d, dep, ws, s);
                     tm.end(s);
                 }
                 break;
@@ -1117,8 +1284,8 @@ extern "C" int hp_stage_backward_noalloc(hp_stage* st, const float* w, const flo
     if (!st) return fail(HP_ERR_ARG, "hp_stage_backward_noalloc: NULL stage");
     // the stage's stream workspace, then the weight-gradient stream's, each
     // starting on a 256-byte boundary
-    const size_t ws_bytes = round_up(std::max<size_t>(st->ws_floats, 64) * sizeof(float), 256);
-    const size_t ws2_bytes = round_up(std::max<size_t>(st->ws2_floats, 64) * sizeof(float), 256);
+    const size_t ws_bytes = workspace_bytes(st->ws_floats);
+    const size_t ws2_bytes = workspace_bytes(st->ws2_floats);
     if (ws_bytes + ws2_bytes > HP_SCRATCH_BYTES)
         return fail(HP_ERR_ARG,
                     "hp_stage_backward_noalloc: the stage needs %zu bytes of workspace, the "

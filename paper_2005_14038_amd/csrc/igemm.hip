@@ -1543,24 +1543,6 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-
-// 16 bytes per lane from a buffer straight into LDS: lane l writes at lds + 16 l
-// (the LDS byte address goes in M0, which must be uniform).  Written as
-// assembly so that the compiler does not track these loads: the kernel waits
-// for them itself (wait_vmcnt before the barrier that publishes a stage), and
-// the compiler's own tracking, which cannot tell the stages apart across the
-// loop's back edge, would wait for every load in flight before the next
-// stage's LDS reads.  The memory clobber keeps LDS accesses on their side.
-__device__ __forceinline__ void buf_load16_lds(__amdgpu_buffer_rsrc_t rs, void* lds, unsigned voff,
-                                               unsigned soff) {
-    const unsigned m0 = (unsigned)(size_t)(lds_ptr_t)lds;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :
-                 : "s"(m0), "v"(voff), "s"(rs), "s"(soff)
-                 : "memory", "m0");
-}
-
 // s_barrier without a memory fence (no wait for outstanding loads); the asm
 // memory clobber keeps the compiler from moving LDS accesses across it
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_barrier" ::: "memory"); }
@@ -2254,8 +2236,28 @@ static bool fast_split(int op, const ConvGeo& g) {
            (op == OP_WGRAD && g.Q % 16 == 0);
 }
 
-GemmPlan plan_gemm(int op, const ConvGeo& g, int bf16, int num_cus, int bias_col, int allow_h16d) {
+// Where an fp32 convolution runs on pieces that lie in memory: see plan_gemm.
+// Every tap's channels are whole k tiles (forward, data gradient) or whole
+// 16-byte groups (weight gradient), and the output columns (rows of the weight
+// gradient) whole 128s, so that tiles are not padded.  With one tap an operand
+// is re-read only N / 128 times and the pass that splits it does not pay, nor
+// does it with few rows.
+bool planes_ok(int op, const ConvGeo& g) {
+    const long lim = (1L << 30) - (1L << 20);             // elements of a plane (< 2 GB)
+    const long x_el = (long)g.N * g.H * g.W * g.C, dy_el = (long)g.N * g.P * g.Q * g.K;
+    if (g.R * g.S < 2 || g.R * g.S > 32 || x_el >= lim || dy_el >= lim ||
+        (long)g.K * g.R * g.S * g.C >= lim || (long)g.N * g.P * g.Q < 2048 || !fits_buffer(g))
+        return false;
+    if (op == OP_FWD) return g.C % 32 == 0 && g.K % 128 == 0;
+    if (op == OP_DGRAD) return g.st == 1 && g.K % 32 == 0 && g.C % 128 == 0;
+    return g.K % 128 == 0 && g.C % 64 == 0;
+}
+
+GemmPlan plan_gemm(int op, const ConvGeo& g, int bf16, int num_cus, int bias_col, int allow_h16d,
+                   long planes_ws) {
     GemmPlan p{};
+    p.planes = (planes_ws > 0 && !bf16 && planes_ok(op, g)) ? 1 : 0;
+    if (p.planes) bias_col = 0;
     p.op = op;
     p.bf16 = bf16;
     p.bias_col = (op == OP_WGRAD) ? bias_col : 0;
@@ -2285,6 +2287,7 @@ GemmPlan plan_gemm(int op, const ConvGeo& g, int bf16, int num_cus, int bias_col
             p.cfg = c0;
         }
     }
+    if (p.planes) p.cfg = (op == OP_WGRAD && g.K % 256 != 0) ? 7 : 6;
     const TileCfg* cp = &kCfgs[p.cfg];
     long tiles = ((p.M + cp->bm - 1) / cp->bm) * ((p.Ncols + cp->bn - 1) / cp->bn);
     int bk = p.h16 ? cp->bkh : (bf16 ? BKH : cp->bk);
@@ -2298,8 +2301,10 @@ GemmPlan plan_gemm(int op, const ConvGeo& g, int bf16, int num_cus, int bias_col
     // occupancy gives them more resident workgroups and reduction chunks.
     if (!bf16) {
         int occ_n = 0;
-        p.split = v4 ? 1 : 0;
-        const KernelRef kn = p.split ? split_kernel(op, p.cfg, fast32) : kernel_for(op, p.cfg, KF_F32_1);
+        p.split = (v4 && !p.planes) ? 1 : 0;
+        const KernelRef kn = p.planes  ? planes_kernel(op, p.cfg)
+                             : p.split ? split_kernel(op, p.cfg, fast32)
+                                       : kernel_for(op, p.cfg, KF_F32_1);
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_n, kn.fn, kn.nt, 0) != hipSuccess ||
             occ_n < 1)
             occ_n = 1;
@@ -2337,7 +2342,8 @@ GemmPlan plan_gemm(int op, const ConvGeo& g, int bf16, int num_cus, int bias_col
     }
     const TileCfg& c = *cp;
     // workgroups resident at once
-    KernelRef kr = p.split ? split_kernel(op, p.cfg, fast32)
+    KernelRef kr = p.planes  ? planes_kernel(op, p.cfg)
+                   : p.split ? split_kernel(op, p.cfg, fast32)
                    : kernel_for(op, p.cfg,
                               p.h16d ? KF_H16D : p.h16k ? KF_H16K
                                      : p.h16 ? KF_H16
@@ -2368,6 +2374,8 @@ GemmPlan plan_gemm(int op, const ConvGeo& g, int bf16, int num_cus, int bias_col
         return r * ((double)ktiles / s + 2.0) + (s > 1 ? (double)wgs * 0.0288 / occ : 0.0);
     };
     auto f32_cut = [&](long cut, long smax) {
+        if (p.planes)
+            smax = std::min(smax, std::max<long>(1, planes_ws / ((long)c.bm * c.bn) / cut));
         double best = f32_cost(cut, 1);
         long sb = 1;
         for (long s = 2; s <= smax; ++s) {
@@ -2477,12 +2485,13 @@ void div_magic(int d, unsigned* m, int* sh) {
 
 bool plan_stats(const GemmPlan& plan, int flags) {
     return (flags & ~EPI_BIAS) == 0 && (plan.bf16 || plan.wide) && !plan.h16d && !plan.fcf &&
-           !plan.fcw;
+           !plan.fcw && !plan.planes;
 }
 
 hipError_t launch_gemm(const GemmPlan& plan, const ConvGeo& g, const float* a, const float* b,
                        float* out, const Epilogue& ep, float* ws, hipStream_t s,
-                       const uint16_t* a16, const uint16_t* b16, const uint16_t* b16t) {
+                       const uint16_t* a16, const uint16_t* b16, const uint16_t* b16t,
+                       const Planes* pl) {
     KArgs k{};
     k.g = g;
     k.a = a;
@@ -2556,7 +2565,18 @@ hipError_t launch_gemm(const GemmPlan& plan, const ConvGeo& g, const float* a, c
         hipLaunchKernelGGL(fcw_kernel, dim3(plan.nwg), dim3(256), 0, s, k);
         return hipGetLastError();
     }
-    const KernelRef kr = plan.split && v4 ? split_kernel(plan.op, plan.cfg, fast32)
+    if (plan.planes) {
+        if (!a16 || !bk16 || !pl || ((((uintptr_t)a16) | ((uintptr_t)bk16)) & 15) != 0)
+            return hipErrorInvalidValue;
+        const long x_el = (long)g.N * g.H * g.W * g.C, dy_el = (long)g.N * g.P * g.Q * g.K;
+        k.b16 = bk16;
+        k.a16s = plan.op == OP_DGRAD ? dy_el : x_el;
+        k.b16s = plan.op == OP_WGRAD ? dy_el : pl->w_plane;
+        k.amax_a = pl->amax_a;
+        k.amax_b = pl->amax_b;
+    }
+    const KernelRef kr = plan.planes       ? planes_kernel(plan.op, plan.cfg)
+                         : plan.split && v4 ? split_kernel(plan.op, plan.cfg, fast32)
                                           : kernel_for(plan.op, plan.cfg, kf);
     void* kargs[] = {&k};
     hipError_t e = hipLaunchKernel(kr.fn, dim3(plan.nwg), dim3(kr.nt), kargs, 0, s);

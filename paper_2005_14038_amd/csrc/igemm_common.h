@@ -36,6 +36,8 @@ constexpr TileCfg kCfgs[] = {
     {64, 128, 16, 32, 64, 64},     // 3: narrow M otherwise (4 waves)
     {64, 64, 16, 32, 32, 64},      // 4: small M and N (4 waves of 32x32)
     {256, 128, 16, 128, 64, 32},   // 5: igemm_h16d_kernel (4 waves)
+    {256, 128, 32, 64, 64, 32},    // 6: the plane kernels (igemm_planes.hip, 8 waves)
+    {128, 256, 32, 64, 64, 32},    // 7: their weight gradient with 128 output rows (8 waves)
 };
 
 struct KArgs {
@@ -56,6 +58,11 @@ struct KArgs {
     int epi;
     const unsigned short* a16;   // bf16 copies of a and b (16-bit operand kernel only)
     const unsigned short* b16;
+    // plane kernels: elements from one plane of a16 / b16 to the next, and the
+    // largest magnitudes their scales follow from
+    long a16s, b16s;
+    const unsigned* amax_a;
+    const unsigned* amax_b;
     // optional: every final output element is also written here rounded to
     // bf16 (nearest even), row-major like out (no bias-gradient column)
     unsigned short* out16;
@@ -460,6 +467,24 @@ __device__ __forceinline__ uintx4 buf_load16(__amdgpu_buffer_rsrc_t rs, unsigned
     return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (int)soff, 0);
 }
 
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
+
+// 16 bytes per lane from a buffer straight into LDS: lane l writes at lds + 16 l
+// (the LDS byte address goes in M0, which must be uniform).  Written as
+// assembly so that the compiler does not track these loads: the kernel waits
+// for them itself (wait_vmcnt before the barrier that publishes a stage), and
+// the compiler's own tracking, which cannot tell the stages apart across the
+// loop's back edge, would wait for every load in flight before the next
+// stage's LDS reads.  The memory clobber keeps LDS accesses on their side.
+__device__ __forceinline__ void buf_load16_lds(__amdgpu_buffer_rsrc_t rs, void* lds, unsigned voff,
+                                               unsigned soff) {
+    const unsigned m0 = (unsigned)(size_t)(lds_ptr_t)lds;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(m0), "v"(voff), "s"(rs), "s"(soff)
+                 : "memory", "m0");
+}
+
 // ---- operand gathers -------------------------------------------------------
 // Each returns VW consecutive elements along the operand's contiguous axis
 // (zero where the element lies outside the problem or in the padding).
@@ -488,5 +513,8 @@ struct KernelRef {
 // The fp32 kernels on split operands (igemm_split.hip) for an operation and
 // tile configuration (fast: igemm_split_kernel's FAST).
 KernelRef split_kernel(int op, int cfg, bool fast);
+
+// The fp32 kernels on operands whose pieces lie in memory (igemm_planes.hip).
+KernelRef planes_kernel(int op, int cfg);
 
 }  // namespace hp

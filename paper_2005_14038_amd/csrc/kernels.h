@@ -28,6 +28,7 @@ struct GemmPlan {
     int h16k;          // h16 and both operands k-major (FWD; DGRAD with stride 1 or 2 and b16t)
     int h16d;          // h16k on the 256 x 128 direct-to-LDS kernel (FWD, stride-1 DGRAD)
     int wide;          // fp32 with the wide (LDS-staged, 16-byte) epilogue: short reductions
+    int planes;        // fp32 on operands split in memory (igemm_planes.hip)
     int split;         // fp32 on split operands (igemm_split.hip)
     int fcf;           // fp32 forward of a fully connected layer on fcf_kernel
     int fcw;           // fp32 weight gradient of a fully connected layer on fcw_kernel
@@ -48,7 +49,10 @@ struct GemmPlan {
 // allow_h16d = 0 keeps the plan off the 256 x 128 direct-to-LDS kernel (whose
 // epilogue writes no column statistics).
 GemmPlan plan_gemm(int op, const ConvGeo& g, int bf16, int num_cus, int bias_col = 0,
-                   int allow_h16d = 1);
+                   int allow_h16d = 1, long planes_ws = 0);
+// planes_ws > 0: fp32 convolutions whose geometry allows it run on operands split
+// into two f16 planes in memory, with at most that many floats of workspace, which launch_gemm then takes as a16 and b16
+// (b16t for the data gradient); plan.planes says whether it did.
 
 // epilogue flags
 enum {
@@ -79,10 +83,34 @@ struct Epilogue {
 // with it a plan with h16k runs on k-major operands.
 // Whether launch_gemm writes Epilogue::stats for this plan and epilogue flags.
 bool plan_stats(const GemmPlan& plan, int flags);
+struct Planes {
+    long w_plane;               // elements from one plane of the weights to the next
+    const unsigned* amax_a;     // the operands' largest magnitudes (launch_split_planes)
+    const unsigned* amax_b;
+};
 hipError_t launch_gemm(const GemmPlan& plan, const ConvGeo& g, const float* a,
                        const float* b, float* out, const Epilogue& ep, float* ws,
                        hipStream_t s, const uint16_t* a16 = nullptr,
-                       const uint16_t* b16 = nullptr, const uint16_t* b16t = nullptr);
+                       const uint16_t* b16 = nullptr, const uint16_t* b16t = nullptr,
+                       const Planes* pl = nullptr);
+
+// p[i] = 0 for n words (a kernel: it may be captured)
+hipError_t launch_clear(unsigned* p, int n, hipStream_t s);
+// The h and l pieces of n values (see igemm_planes.hip) as planes of f16:
+// dst[q * n + i] = piece q of src[i]; *amax (0 before) takes the bits of their
+// largest finite magnitude.
+hipError_t launch_split_planes(const float* src, uint16_t* dst, size_t n, unsigned* amax,
+                               hipStream_t s);
+// The same for convolution weights, in their own order ([K][RS][C], at
+// dst + L.dst) and transposed ([C][RS][K], at dst_t + L.dst), planes `plane` elements
+// apart, amax[i] for layer i: every layer of a device table whose tile0 are prefix sums of wt_tiles.
+struct WpLayer {
+    long off, dst;
+    int K, RS, C, tile0;
+};
+hipError_t launch_split_weights(const float* src, uint16_t* dst, uint16_t* dst_t, long plane,
+                                const WpLayer* table, int nlayers, int tiles, unsigned* amax,
+                                hipStream_t s);
 
 // dst[i] = bf16(src[i]) (round to nearest even), n elements
 hipError_t launch_cast_bf16(const float* src, uint16_t* dst, size_t n, hipStream_t s);

@@ -42,6 +42,13 @@ CONV = [
     (2, 12, 12, 20, 16, 3, 1, 1, False),   # C % 16 != 0 forward, FAST data gradient
     (2, 14, 14, 16, 32, 7, 1, 3, False),   # FAST 7 x 7 taps (the largest the tap stepping takes)
     (2, 12, 12, 16, 32, 5, 1, 2, True),    # FAST 5 x 5 taps
+    # fp32 on operands split in memory (at least 2048 output pixels)
+    (2, 32, 32, 128, 128, 3, 1, 1, True),  # exactly 2048, all three; 128-row weight gradient
+    (3, 27, 29, 64, 128, 3, 1, 1, True),   # ragged M and k tiles; narrow data gradient beside them
+    (3, 53, 55, 32, 128, 3, 2, 1, False),  # strided forward alone
+    (4, 25, 23, 128, 256, 3, 1, 1, False), # 256-row weight gradient, ragged reduction
+    (1, 50, 47, 192, 160, 2, 1, 0, True),  # even taps, no padding, K a multiple of 32 only
+    (1, 49, 45, 128, 128, 5, 1, 2, False), # 25 taps
 ]
 
 
@@ -64,6 +71,40 @@ def test_conv(dev, case, dtype):  # noqa: F811
     assert_close(g["y"], r["y"], tol, "forward")
     assert_close(g["grad"], r["grad"], tol, "weight gradient")
     assert_close(g["dx"], r["dx"], tol, "data gradient")
+
+
+def test_conv_split_operands_range(dev):  # noqa: F811
+    """fp32 on operands split in memory, one scale per tensor: images 2^-10, 2^-20 and
+    2^-26 below the largest keep the fp32 tolerance, each by itself."""
+    case = (4, 25, 23, 128, 128, 3, 1, 1, False)
+    net, B = conv_net(case)
+    w = oracle_weights(net, 13)
+    x, _, dy = make_inputs(net, B, 14)
+    scale = np.array([1, 2.0 ** -10, 2.0 ** -20, 2.0 ** -26], np.float32).reshape(-1, 1, 1, 1)
+    x, dy = x * scale, dy * scale
+    g = run_gpu(net, B, w, x, None, dy, True)
+    r = run_oracle(net, w, x, None, dy, True)
+    for i in range(B):
+        assert_close(g["y"][i] / scale[i], r["y"][i] / scale[i], FP32_TOL, f"forward, image {i}")
+        assert_close(g["dx"][i] / scale[i], r["dx"][i] / scale[i], FP32_TOL,
+                     f"data gradient, image {i}")
+    assert_close(g["grad"], r["grad"], FP32_TOL, "weight gradient")
+
+
+def test_conv_split_operands_infinity(dev):  # noqa: F811
+    """An infinite input reaches the outputs that read it and no other."""
+    case = (4, 25, 23, 128, 128, 3, 1, 1, False)
+    net, B = conv_net(case)
+    w = oracle_weights(net, 15)
+    x, _, dy = make_inputs(net, B, 16)
+    x[1, 5, 7, 3] = np.inf
+    g = run_gpu(net, B, w, x, None, dy, True)
+    r = run_oracle(net, w, x, None, dy, True)
+    for key in ("y", "grad", "dx"):
+        got, ref = np.asarray(g[key]).reshape(-1), np.asarray(r[key]).reshape(-1)
+        ok = np.isfinite(ref)
+        assert np.array_equal(np.isfinite(got), ok), key
+        assert_close(got[ok], ref[ok], FP32_TOL, key)
 
 
 def random_conv(seed):
